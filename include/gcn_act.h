@@ -57,8 +57,10 @@ extern "C" {
 #define GCN_LOSS_SIGMOID_BCE 1   /* labels: uint8[n*C] 0/1, row-major     */
 
 #define GCN_PREC_FP32 0          /* dense products of fp32 operands: each split
-                                    exactly into three bf16 values, fp32
-                                    accumulation                         */
+                                    exactly (any finite value) into three
+                                    bf16 values, six of their nine products
+                                    formed (the others are below 2^-23 of
+                                    the whole), fp32 accumulation        */
 #define GCN_PREC_BF16 1          /* bf16 MFMA operands, fp32 accumulation */
 
 #define GCN_AGG_MEAN 0           /* Y = D^-1 A X        (forward, Eq. 1)   */

@@ -93,6 +93,58 @@ def test_classifier_products(n, K, C):
     torch.cuda.synchronize()
 
 
+def _powers(n, width, e, seed):
+    """+-[1, 2) x 2^e, exact in float32 down to its last subnormal bit."""
+    x = (torch.rand(n, width, generator=torch.Generator().manual_seed(seed),
+                    dtype=torch.float64) * 2 - 1)
+    return torch.copysign(1 + x.abs(), x).mul(2.0 ** e).float().cuda()
+
+
+# operands down to the smallest subnormals times large ones: the split keeps
+# every bit of any finite value
+@pytest.mark.parametrize("e", [-100, -112, -118, -126, -130, -140])
+@pytest.mark.parametrize("n,K,C", [(300, 40, 24), (65, 130, 7)])
+def test_tiny_operands(e, n, K, C):
+    need_gpu()
+    say("tiny operands", e, n, K, C)
+    from paper_2001_02498_amd import gcn
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, max(K, C), n))
+    f = min(-e, 110)
+    d = lambda t: t.double()  # noqa: E731
+    for a, b in ((e, f), (f, e)):
+        H, W = empty(n, K, (K + 3) // 4 * 4), _powers(K, C, b, 2)
+        H.copy_(_powers(n, K, a, 1).abs())
+        Z, dZ, G = empty(n, C, (C + 3) // 4 * 4), empty(n, C, (C + 3) // 4 * 4), empty(
+            n, K, (K + 3) // 4 * 4)
+        gcn.classifier_fwd(H, K, W, None, Z, ws)
+        _close(Z, d(H) @ d(W), K)
+        dZ.copy_(_powers(n, C, a, 3))
+        dW, W0 = torch.empty_like(W), d(W)
+        gcn.classifier_bwd(dZ, C, H, K, W.clone(), None, 0.0, G, dW, None, ws)
+        _close(G, d(dZ) @ W0.T, C)
+        dZ.copy_(_powers(n, C, b, 4))
+        gcn.classifier_bwd(dZ, C, H, K, W, None, 0.0, None, dW, None, ws)
+        _close(dW, d(H).T @ d(dZ), n)
+    torch.cuda.synchronize()
+
+
+# products below the smallest normal value: one rounding to a multiple of
+# 2^-149 per K step (and one per K slice) and nothing else at that size
+@pytest.mark.parametrize("e", [-64, -68, -72])
+def test_tiny_products(e):
+    need_gpu()
+    say("tiny products", e)
+    from paper_2001_02498_amd import gcn
+    n, K, C = 300, 32, 24
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, K, n))
+    H, W, Z = _powers(n, K, e, 1), _powers(K, C, e, 2), empty(n, C)
+    gcn.classifier_fwd(H, K, W, None, Z, ws)
+    ref = H.double() @ W.double()
+    bound = 0.5 * 2.0 ** -149 + 8 * 2.0 ** -24 * (H.double().abs() @ W.double().abs())
+    assert ((Z.double() - ref).abs() <= bound).all()
+    torch.cuda.synchronize()
+
+
 # a bf16 part of an infinity, a NaN or a value above the largest bf16 is not
 # finite: those outputs are recomputed as fp32 products, the others are not
 # touched by them
