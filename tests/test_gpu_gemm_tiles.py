@@ -93,6 +93,48 @@ def test_classifier_products(n, K, C):
     torch.cuda.synchronize()
 
 
+# sums of a few terms (one or two are fp32 products, more are split): a product of one term is the rounded product, and
+# K terms are rounded K times at most at the size of their sum of magnitudes
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("n,C", [(1000, 30), (129, 130)])
+def test_short_sums(K, n, C):
+    need_gpu()
+    say("short sums", K, n, C)
+    from paper_2001_02498_amd import gcn
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, max(n, C), max(n, C)))
+    d = lambda t: t.double()  # noqa: E731
+    one = K == 1
+
+    def check(got, A, B):
+        ref = d(A) @ d(B)
+        if one:
+            assert torch.equal(got, ref.float())
+        assert ((d(got) - ref).abs() <= K * 2.0 ** -24 * (d(A).abs() @ d(B).abs())).all()
+
+    H, W = empty(n, K, 8), _randn(K, C, seed=1)
+    H.copy_(_randn(n, K).abs() + 0.01)
+    Z = empty(n, C, (C + 3) // 4 * 4)
+    gcn.classifier_fwd(H, K, W, None, Z, ws)
+    check(Z, H, W)
+    # the input gradient sums over the K classes, the weight gradient over the K rows
+    W, dZ, G = _randn(n, K, seed=3), empty(C, K, 8), empty(C, n, (n + 3) // 4 * 4)
+    H = empty(C, n, (n + 3) // 4 * 4)
+    H.fill_(1.0)
+    dZ.copy_(_randn(C, K, seed=4))
+    W0 = W.clone()
+    gcn.classifier_bwd(dZ, K, H, n, W, None, 0.0, G, None, None, ws)
+    check(G, dZ, W0.T)
+    H, dZ = empty(K, n, (n + 3) // 4 * 4), empty(K, C, (C + 3) // 4 * 4)
+    H.copy_(_randn(K, n, seed=5))
+    dZ.copy_(_randn(K, C, seed=6))
+    W, b = torch.zeros(n, C, device="cuda"), torch.zeros(C, device="cuda")
+    dW, db = torch.empty_like(W), torch.empty_like(b)
+    gcn.classifier_bwd(dZ, C, H, n, W, b, 0.0, None, dW, db, ws)
+    check(dW, H.T, dZ)
+    check(db[None], torch.ones(1, K, device="cuda"), dZ)
+    torch.cuda.synchronize()
+
+
 def _powers(n, width, e, seed):
     """+-[1, 2) x 2^e, exact in float32 down to its last subnormal bit."""
     x = (torch.rand(n, width, generator=torch.Generator().manual_seed(seed),
