@@ -188,8 +188,8 @@ def test_tiny_products(e):
 
 
 # a bf16 part of an infinity, a NaN or a value above the largest bf16 is not
-# finite: those outputs are recomputed as fp32 products, the others are not
-# touched by them
+# finite: the outputs it enters are recomputed as fp32 products, the others
+# stay bit for bit what they are without it
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
 @pytest.mark.parametrize("n,K,C", [(300, 100, 24), (8100, 40, 512)])
 def test_non_finite(bad, n, K, C):
@@ -212,7 +212,7 @@ def test_non_finite(bad, n, K, C):
         assert torch.equal(torch.isnan(Z[70]).cpu(), torch.isnan(want).cpu())
         fin = ~torch.isnan(want)
         assert torch.equal(Z[70][fin].double(), want[fin])
-    _close(Z[others], ref[others].double(), K)
+    assert torch.equal(Z[others], ref[others])
     torch.cuda.synchronize()
 
 
