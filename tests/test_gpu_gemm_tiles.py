@@ -216,6 +216,106 @@ def test_non_finite(bad, n, K, C):
     torch.cuda.synchronize()
 
 
+def _redone(got, want, with_inf, clean, bad, K):
+    """`want` (64 bits) holds a bad operand's outputs, `with_inf` those of an
+    infinity in its place (non-finite where it enters), `clean` the call
+    without it."""
+    if np.isfinite(bad):
+        assert torch.isfinite(got).all()
+        _close(got, want, K)
+    else:
+        assert torch.equal(torch.isnan(got), torch.isnan(want))
+        inf = torch.isinf(want)
+        assert torch.equal(got[inf].double(), want[inf])
+    other = torch.isfinite(with_inf)
+    assert not other.all()
+    assert torch.equal(got[other], clean[other])
+
+
+# the same in the backward products: K-major operands with the row of ones and
+# K slices (the gradients), K-concatenated operands with the weights as [n][k]
+# (the input gradient); in the classifier's the weight rows are not aligned
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("n,F,h", [(300, 33, 20), (8100, 97, 128)])
+@pytest.mark.parametrize("where", ["H", "G", "W"])
+def test_non_finite_layer_bwd(bad, n, F, h, where):
+    need_gpu()
+    say("non-finite layer_bwd", bad, n, F, h, where)
+    case = _case(n)
+    gcn = case.gcn
+    ws = gcn.alloc_ws(gcn.scratch_bytes(case.dg, max(F, 2 * h)))
+    H, AH = empty(n, F, (F + 3) // 4 * 4), empty(n, F, (F + 3) // 4 * 4)
+    H.copy_(_randn(n, F) * 0.1)      # 3e38 times them is finite
+    AH.copy_(_randn(n, F, seed=1) * 0.1)
+    W0 = [_randn(F, h, seed=2 + i) * 1e-3 for i in range(2)]
+    G, T = empty(n, 2 * h), empty(n, h)
+    G.copy_(_randn(n, 2 * h, seed=4) * 1e-5)
+    row, col = n - 17, h + 3
+
+    def call():
+        W = [w.clone() for w in W0]
+        out = [empty(n, F, (F + 3) // 4 * 4)] + [torch.empty(F, h, device="cuda") for _ in
+                                                 range(2)] + [torch.empty(2 * h, device="cuda")]
+        gcn.aggregate(case.dg, gcn.AGG_TRANSPOSED, G[:, h:], T, ws)
+        gcn.layer_bwd(case.dg, G, H, AH, *W, torch.zeros(2 * h, device="cuda"), 0.0, *out, ws)
+        return out
+
+    def spoil(x):
+        t, i, j = {"H": (H, row, 5), "G": (G, row, col), "W": (W0[1], 5, 3)}[where]
+        t[i, j] = x
+
+    def exact():
+        d = lambda t: t.double()  # noqa: E731
+        gin = d(G[:, :h]) @ d(W0[0]).T + d(T) @ d(W0[1]).T
+        return [torch.where(H > 0, gin, 0.0), d(H).T @ d(G[:, :h]), d(AH).T @ d(G[:, h:]),
+                d(G).sum(0)]
+
+    clean = call()
+    spoil(np.inf)
+    call()     # (T)
+    with_inf = exact()
+    spoil(bad)
+    got = call()
+    want = exact()
+    entered = {"H": [1], "G": [0, 2, 3], "W": [0]}[where]
+    for i, K in enumerate((2 * h, n, n, n)):
+        if i in entered:
+            _redone(got[i], want[i], with_inf[i], clean[i], bad, K)
+        elif i:
+            assert torch.equal(got[i], clean[i])
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("n,K,C", [(300, 100, 7), (8100, 260, 41)])
+def test_non_finite_classifier_bwd(bad, n, K, C):
+    need_gpu()
+    say("non-finite classifier_bwd", bad, n, K, C)
+    from paper_2001_02498_amd import gcn
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, max(K, C), n))
+    H, dZ = empty(n, K), empty(n, C, (C + 3) // 4 * 4)
+    H.copy_(_randn(n, K).abs() * 0.1)
+    dZ.copy_(_randn(n, C, seed=1) * 1e-5)
+    W0 = _randn(K, C, seed=2) * 1e-3
+
+    def call():
+        out = [empty(n, K), torch.empty(K, C, device="cuda"), torch.empty(C, device="cuda")]
+        gcn.classifier_bwd(dZ, C, H, K, W0.clone(), torch.zeros(C, device="cuda"), 0.0, *out, ws)
+        return out
+
+    def exact():
+        d = lambda t: t.double()  # noqa: E731
+        return [d(dZ) @ d(W0).T, d(H).T @ d(dZ), d(dZ).sum(0)]
+
+    clean = call()
+    dZ[n - 17, 3] = np.inf
+    with_inf = exact()
+    dZ[n - 17, 3] = bad
+    for got, want, wi, c, k in zip(call(), exact(), with_inf, clean, (C, n, n)):
+        _redone(got, want, wi, c, bad, k)
+    torch.cuda.synchronize()
+
+
 # the update takes four weights per thread where every pointer allows 16-byte
 # accesses, one otherwise: the same sums either way
 @pytest.mark.parametrize("C", [24, 25])
