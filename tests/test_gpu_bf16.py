@@ -74,7 +74,8 @@ def test_classifier_bf16(n, K, C, bias):
 
 
 @pytest.mark.parametrize("n,F,h,bias", [(777, 50, 36, False), (1024, 300, 128, True),
-                                        (513, 1024, 132, False), (1000, 256, 128, False)])
+                                        (513, 1024, 132, False), (1000, 256, 128, False),
+                                        (8200, 64, 516, True)])   # 128 x 128 tiles
 def test_layer_fwd_bf16(n, F, h, bias):
     need_gpu()
     say("layer_fwd bf16", n, F, h, bias)
