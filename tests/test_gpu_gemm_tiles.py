@@ -316,17 +316,19 @@ def test_non_finite_classifier_bwd(bad, n, K, C):
     torch.cuda.synchronize()
 
 
-# the update takes four weights per thread where every pointer allows 16-byte
-# accesses, one otherwise: the same sums either way
-@pytest.mark.parametrize("C", [24, 25])
+# the update takes four weights per thread in launches of 2^19 weights or more
+# where every pointer allows 16-byte accesses, one otherwise: the same sums
+# either way
+@pytest.mark.parametrize("K,C", [(68, 24), (68, 25), (1024, 512), (1024, 513), (1022, 512)])
 @pytest.mark.parametrize("shift", [0, 1])
-def test_update_alignment(C, shift):
+def test_update_alignment(K, C, shift):
     need_gpu()
-    say("update", C, shift)
+    say("update", K, C, shift)
     from paper_2001_02498_amd import gcn
-    n, K = 513, 68
-    ws = gcn.alloc_ws(gcn.scratch_bytes(None, K, n))
-    H, dZ = _randn(n, K), empty(n, C, (C + 3) // 4 * 4)
+    n = 513
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, max(K, C), n))
+    H, dZ = empty(n, K), empty(n, C, (C + 3) // 4 * 4)
+    H.copy_(_randn(n, K))
     dZ.copy_(_randn(n, C, seed=3))
     W0, b0 = _randn(K, C, seed=1), _randn(C, seed=2)
     W = torch.zeros(K * C + shift, device="cuda")[shift:].view(K, C)
