@@ -346,10 +346,11 @@ int do_classifier_fwd(const char* fn, int32_t n, int32_t K, int32_t C,
 }
 
 // dW = A^T B over K = n rows, K split into slices at `part` (`shape`: the
-// fp32 kernel's tile shape).
+// fp32 kernel's tile shape), as `like` is where that is given.
 GemmProblem dw_problem(int32_t n, int32_t Mw, bool ones, int32_t N,
                        const float* A, int64_t lda, const float* B, int64_t ldb,
-                       float* part, int32_t nprob, bool bf16, int32_t* shape) {
+                       float* part, int32_t nprob, bool bf16, int32_t* shape,
+                       const GemmProblem* like = nullptr) {
     GemmProblem p = gp_zero();
     p.M = Mw + (ones ? 1 : 0);
     p.N = N;
@@ -359,11 +360,15 @@ GemmProblem dw_problem(int32_t n, int32_t Mw, bool ones, int32_t N,
     p.ones_row = ones ? 1 : 0;
     p.B0 = p.B1 = B;
     p.ldb0 = p.ldb1 = ldb;
-    if (bf16)
+    if (like) {
+        p.splits = like->splits;
+        p.kchunk = like->kchunk;
+    } else if (bf16) {
         gemm_split_plan_tiles((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * nprob, p.K,
                               &p.splits, &p.kchunk);
-    else
+    } else {
         gemm_plan(p.M, p.N, p.K, nprob, true, shape, &p.splits, &p.kchunk);
+    }
     p.C = part;
     p.ldc = r4(N);
     p.part_stride = (int64_t)p.M * p.ldc;
@@ -544,7 +549,7 @@ int do_layer_bwd(const char* fn, const gcn_dgraph* g, int32_t F, int32_t h,
     float* part1 = part0 + sp.gemm_part_floats;
     const bool ones = bias != nullptr;
     b.p[0] = dw_problem(n, F, ones, h, H_in, ld_in, G, ldg, part0, 2, bf16, &b.shape);
-    b.p[1] = dw_problem(n, F, ones, h, AH, ld_ah, G + h, ldg, part1, 2, bf16, &b.shape);
+    b.p[1] = dw_problem(n, F, ones, h, AH, ld_ah, G + h, ldg, part1, 2, bf16, &b.shape, &b.p[0]);
     if (c) {
         for (int i = 0; i < 2; ++i) {
             b.p[i].hA0 = b.p[i].hA1 = i == 0 ? c->Hin : c->AH;
@@ -676,7 +681,7 @@ int do_layer_bwd_narrow(const char* fn, const gcn_dgraph* g, int32_t F, int32_t 
     float* part0 = part_region(ws, sp, region);
     float* part1 = part0 + sp.gemm_part_floats;
     b.p[0] = dw_problem(n, F, false, h, H_in, ld_in, G, ldg, part0, 2, bf16, &b.shape);
-    b.p[1] = dw_problem(n, F, false, h, H_in, ld_in, T, ldt, part1, 2, bf16, &b.shape);
+    b.p[1] = dw_problem(n, F, false, h, H_in, ld_in, T, ldt, part1, 2, bf16, &b.shape, &b.p[0]);
     if (c) {
         for (int i = 0; i < 2; ++i) {
             b.p[i].hA0 = b.p[i].hA1 = c->Hin;

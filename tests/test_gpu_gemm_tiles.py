@@ -32,11 +32,14 @@ def _randn(*shape, seed=0):
     return torch.randn(*shape, device="cuda", generator=g)
 
 
-# the planned shapes: 160 x 128 (n 10,001), 128 x 128 (8,065), 128 x 64
-# (6,785), 64 x 64 (the rest); the rows, columns and K end one past a tile,
-# one short of one, and on one
+# the planned shapes of the forward product: 160 x 128 (n 10,001), 128 x 128
+# (8,065), 128 x 64 (6,785), 64 x 64 (to 17), 64 x 64 with two buffers (the
+# rest: six, eight and eight K steps, the last one whole or not; the input
+# gradients' operands concatenated on a step and off it); the rows, columns and
+# K end one past a tile, one short of one, and on one
 @pytest.mark.parametrize("n,F,h", [(10001, 33, 512), (8065, 64, 512), (6785, 97, 256),
-                                   (65, 1, 4), (63, 31, 20), (128, 32, 64), (17, 130, 68)])
+                                   (65, 1, 4), (63, 31, 20), (128, 32, 64), (17, 130, 68),
+                                   (300, 192, 96), (257, 225, 100), (1000, 250, 132)])
 @pytest.mark.parametrize("bias", [False, True])
 def test_layer_products(n, F, h, bias):
     need_gpu()
@@ -71,9 +74,9 @@ def test_layer_products(n, F, h, bias):
 
 
 # unaligned rows of W_cls (C % 4 != 0), one column tile and two, with and
-# without K slices
+# without K slices, one buffer and two (n 16,000)
 @pytest.mark.parametrize("n,K,C", [(1000, 256, 7), (129, 1024, 41), (4097, 512, 121),
-                                   (2000, 64, 130), (33, 36, 1)])
+                                   (2000, 64, 130), (33, 36, 1), (16000, 228, 41)])
 def test_classifier_products(n, K, C):
     need_gpu()
     say("cls tiles", n, K, C)
