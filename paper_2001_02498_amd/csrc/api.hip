@@ -320,7 +320,7 @@ int do_classifier_fwd(const char* fn, int32_t n, int32_t K, int32_t C,
         const int64_t tiles = (int64_t)((n + 127) / 128) * ((C + 127) / 128);
         if (tiles < 192) gemm_split_plan_tiles(tiles, K, &splits, &kchunk);
     } else {
-        gemm_plan(n, C, K, 1, true, &b.shape, &splits, &kchunk);
+        gemm_plan(n, C, K, 1, A_MK, true, &b.shape, &splits, &kchunk);
     }
     if (splits > 1) {
         p.splits = splits;
@@ -367,7 +367,7 @@ GemmProblem dw_problem(int32_t n, int32_t Mw, bool ones, int32_t N,
         gemm_split_plan_tiles((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * nprob, p.K,
                               &p.splits, &p.kchunk);
     } else {
-        gemm_plan(p.M, p.N, p.K, nprob, true, shape, &p.splits, &p.kchunk);
+        gemm_plan(p.M, p.N, p.K, nprob, A_KM, true, shape, &p.splits, &p.kchunk);
     }
     p.C = part;
     p.ldc = r4(N);

@@ -116,8 +116,8 @@ struct GemmBatch {
 // non-empty when K > 0.
 void gemm_split_plan_tiles(int64_t tiles, int32_t K, int32_t* splits, int32_t* kchunk);
 // The same for an fp32 launch of `nprob` M x N products, with its tile shape.
-void gemm_plan(int32_t M, int32_t N, int32_t K, int32_t nprob, bool may_split, int32_t* shape,
-               int32_t* splits, int32_t* kchunk);
+void gemm_plan(int32_t M, int32_t N, int32_t K, int32_t nprob, ALayout al, bool may_split,
+               int32_t* shape, int32_t* splits, int32_t* kchunk);
 
 // Which product of the step a launch computes (its own kernel name and
 // timing class; the code depends only on layouts and epilogue).
