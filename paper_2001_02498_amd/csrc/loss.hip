@@ -128,9 +128,9 @@ __global__ __launch_bounds__(256) void loss_kernel(
 }
 
 // Fixed-order reduction: thread t sums rows t, t+1024, ...; then a tree. One
-// workgroup, so bound by the latency of its loads: 1,024 threads with four
-// rows each in flight take 10,000 rows in three rounds (4.0 us; 256
-// threads with eight 6.8 us).
+// workgroup, so bound by the latency of its loads: 1,024 threads take 10,000
+// rows in two rounds of four rows in flight and one or two single ones (4.0 us;
+// 256 threads with eight in flight 6.0 us).
 constexpr int kMeanThreads = 1024;
 
 __global__ __launch_bounds__(kMeanThreads) void mean_kernel(int n,
