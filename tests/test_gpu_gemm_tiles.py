@@ -173,6 +173,23 @@ def test_tiny_operands(e, n, K, C):
     torch.cuda.synchronize()
 
 
+# sums that overflow only by the split's scale are fp32 products: K of them are
+# rounded K times at most at the size of their sum of magnitudes
+@pytest.mark.parametrize("a,b", [(47, 49), (60, 60), (113, -20), (126, -126), (-130, 126)])
+@pytest.mark.parametrize("n,K,C", [(300, 40, 24), (65, 130, 7)])
+def test_large_operands(a, b, n, K, C):
+    need_gpu()
+    say("large operands", a, b, n, K, C)
+    from paper_2001_02498_amd import gcn
+    ws = gcn.alloc_ws(gcn.scratch_bytes(None, max(K, C), n))
+    H, W, Z = empty(n, K, (K + 3) // 4 * 4), _powers(K, C, b, 2), empty(n, C, (C + 3) // 4 * 4)
+    H.copy_(_powers(n, K, a, 1))
+    gcn.classifier_fwd(H, K, W, None, Z, ws)
+    ref, size = H.double() @ W.double(), H.double().abs() @ W.double().abs()
+    assert ((Z.double() - ref).abs() <= K * 2.0 ** -24 * size).all()
+    torch.cuda.synchronize()
+
+
 # products below the smallest normal value: one rounding to a multiple of
 # 2^-149 per K step (and one per K slice) and nothing else at that size
 @pytest.mark.parametrize("e", [-64, -68, -72])
